@@ -113,18 +113,37 @@ int validate_config(const lukv_config* cfg, HostCfg* out) {
     if (g.chunk_keys < 1024 && n_wgs(1024) >= 1024) g.chunk_keys = 1024;
     if (g.chunk_keys == 1024 && n_wgs(2048) >= 2048) g.chunk_keys = 2048;
     // Calls that leave the chip idle at that size cut the work finer, in ways that leave every result
-    // bit for bit the same.  The accumulation kernel takes shorter chunks (a key's score is a sum over
-    // rows, whatever its neighbours), as long as there are no more than 512 workgroups: one layer of
-    // 4001 tokens 42.4 -> 39.3 us a call, of 24000 and more no gain.  Not below a quarter of the
-    // statistics chunk, which bounds the range entries in the workspace.
+    // bit for bit the same.  The accumulation kernel takes a half or a quarter of a chunk a workgroup (a
+    // key's score is a sum over rows, whatever its neighbours; a quarter of a statistics chunk bounds the
+    // range entries in the workspace), while some units would be idle (256 pieces at most) and all the
+    // smaller pieces, with the few extra workgroups of the allocation, are still resident at once: one a
+    // unit in float32 at 128 elements, two otherwise, three in bf16 at 64 elements.  A second round
+    // costs more than shorter pieces give (20000 tokens of 4 heads in float32: 57 us uncut, 63 with 316
+    // pieces); beyond 128 rows a piece is work enough that the allocation's workgroups don't matter.
+    // Above 256 pieces also only where most of a chunk has keys (256 heads of 310 tokens: 79 -> 84).
+    // One layer of 4001 tokens 43.1 us uncut, 38.7 in pieces of 128 keys; 8 heads of 131072, 16 rows:
+    // 60.9 -> 52.7; 24000 tokens and more of 8 heads: uncut.
     g.accum_keys = g.chunk_keys;
-    while (g.accum_keys > 128 && g.accum_keys > g.chunk_keys / 4 && n_wgs(g.accum_keys / 2) <= 512) g.accum_keys /= 2;
+    auto n_pieces = [&](int keys) {
+      int64_t n = 0;
+      for (int s = 0; s < cfg->n_seqs; ++s) n += (out->seq.cu[s + 1] - out->seq.cu[s] - g.window + keys - 1) / keys;
+      return n * g.n_kv_heads * g.n_layers;
+    };
+    const int most = g.rows > 128 ? (g.f32 ? 448 : 512) : g.head_dim == 64 && !g.f32 ? 704 : g.head_dim == 128 && g.f32 ? 256 : 448;
+    while (g.accum_keys > 128 && g.accum_keys > g.chunk_keys / 4) {
+      const int64_t now = n_pieces(g.accum_keys), cut = n_pieces(g.accum_keys / 2);
+      if (now > 256 || cut > most || 2 * cut < 3 * now) break;
+      if (cut > 256 && 4 * (max_len - g.window) < 3 * g.accum_keys) break;
+      g.accum_keys /= 2;
+    }
+    g.accum_parts = g.chunk_keys / g.accum_keys;
     // The statistics kernel cannot (a granule's sum runs over its keys in order), so one workgroup
     // takes one block of 32 rows per wave group (not fewer groups: they fix the order of the keys), and
-    // the chunk's keys come from the caches for all but the first:
-    // 4001 tokens 39.3 -> 35.8 us, 12000 (768 workgroups) 45.1 -> 43.2, 16384 (1024) 46.4 -> 47.7.
+    // the chunk's keys come from the caches for all but the first.  Up to 768 workgroups, three a unit
+    // (the registers of that form): 4001 tokens 38.7 -> 34.7 us, 12000 (768 workgroups) 45.1 -> 43.2,
+    // 16384 (1024) 46.4 -> 47.7.
     const bool by_rows = n_wgs(g.chunk_keys) * g.blocks_per_group <= 768;
-    g.row_parts = by_rows ? g.blocks_per_group : 1;
+    g.row_parts = by_rows ? g.blocks_per_group : 0;
     g.part_blocks = by_rows ? 1 : g.blocks_per_group;
   }
   out->n_hi = cfg->n_seqs * g.n_layers * g.n_kv_heads;
@@ -148,7 +167,8 @@ WsLayout make_layout(const HostCfg& hc, int32_t n_grid, bool alloc_only) {
   w.n_hi = hc.n_hi;
   w.max_chunks = g.accum_keys > 0 ? (hc.max_len + g.accum_keys - 1) / g.accum_keys : 0;
   w.max_slices = (hc.max_len + kSliceElems - 1) / kSliceElems;
-  w.range_stride = w.max_chunks > w.max_slices ? w.max_chunks : w.max_slices;
+  const int32_t n_range = w.max_chunks * range_per(g);
+  w.range_stride = n_range > w.max_slices ? n_range : w.max_slices;
   w.rows_padded = g.row_blocks * 32;
   int64_t off = 0;
   auto take = [&](int64_t bytes) { const int64_t o = off; off = align_up(off + bytes, 256); return o; };

@@ -39,7 +39,8 @@ struct Geom {
   int32_t total_tokens;
   int32_t chunk_keys;  // keys one workgroup of the statistics kernel streams (multiple of a granule)
   int32_t accum_keys;  // keys one workgroup of the accumulation kernel streams (multiple of 128)
-  int32_t row_parts;   // workgroups of the statistics kernel that share a chunk, each with its own rows
+  int32_t accum_parts; // chunk_keys / accum_keys: workgroups of that kernel that share a chunk
+  int32_t row_parts;   // workgroups of the statistics kernel that share a chunk, each with its own rows (0: plain grid)
   int32_t part_blocks; // row blocks of a wave group of that kernel
   int64_t sl, sh, st;     // K/V strides (elements)
   int64_t qsl, qsh, qst;  // Q strides (elements)
@@ -51,7 +52,7 @@ struct Geom {
 struct WsLayout {
   int64_t alloc_vertex;          // i32 [n_problems * n_heads * n_grid]
   int64_t hist;                  // u32 [n_hi * max_slices * kHistBins / 2] packed 16-bit suffix counts
-  int64_t range;                 // float2 [n_hi * range_stride] (min, max) of the metric per chunk of the accumulation kernel (or slice)
+  int64_t range;                 // float2 [n_hi * range_stride] (min, max) of the metric per wave (or piece) of the accumulation kernel, or per slice
   int64_t head_dig;              // uint2 [n_hi] first digit of the selection: (base key, shift)
   int64_t by_bin;                // u64 [n_layers * n_kv_heads * total_tokens] (key, position) by slice and bin
   int64_t cand;                  // u64, same shape: threshold candidates of a head beyond the LDS list
@@ -69,6 +70,10 @@ struct WsLayout {
   int64_t total;
   int32_t n_hi, max_chunks, max_slices, range_stride, rows_padded;
 };
+
+// Range entries per workgroup of the accumulation kernel: one per wave, or one in all where several
+// workgroups share a chunk (at most four do, so that neither takes more room than the other).
+inline int32_t range_per(const Geom& g) { return g.accum_parts > 1 ? 1 : 4; }
 
 struct HostCfg {
   Geom g;

@@ -194,11 +194,44 @@ __device__ __forceinline__ int64_t spread_item(const AllocIO& aio, int kp, int n
   return (wave < kp && item < n_knots) ? item : -1;
 }
 
+// Row form of a grid, for calls of few workgroups: the chunks of keys of all heads in one row, the
+// `parts` workgroups that share a chunk (its rows in the statistics kernel, its pieces in the
+// accumulation kernel) eight apart, next to each other on one XCD, so that both kernels read a chunk's
+// keys into the same L2.  Chunks are numbered tile by tile, all heads of a tile together: a short last
+// tile of every head then falls on all XCDs alike (head by head, two tiles a head, the short ones all
+// fall on every other XCD).  Head by head where the statistics kernel is not in this form: its plain
+// grid is numbered that way.
+// x / n is (x * (2^20 / n + 1)) >> 20 while x * n < 2^20, so the form is for up to kRowChunks chunks
+// (six divisions by the hardware's reciprocal made the prologue 0.5 us longer).
+constexpr int kRowChunks = 768;
+struct RowForm { unsigned parts, n, r_parts, r_n, r_heads; int by_tile; };
+
+static RowForm row_form(const Geom& g, int parts, int n_tiles, bool by_tile) {
+  auto r = [](int n) { return (1u << 20) / (unsigned)n + 1u; };
+  const int n = by_tile ? g.n_kv_heads * g.n_layers : n_tiles;
+  return RowForm{(unsigned)parts, (unsigned)n, r(parts), r(n), r(g.n_kv_heads), by_tile};
+}
+
+// False: padding to whole eights.
+__device__ __forceinline__ bool row_chunk(const Geom& g, const RowForm& rf, int n_tiles, int block, int& tile, int& part,
+                                          int& kvh, int& layer) {
+  const unsigned b = (unsigned)block, eight = ((b >> 3) * rf.r_parts) >> 20;
+  const unsigned chunk = eight * 8u + (b & 7u), d = (chunk * rf.r_n) >> 20, m = chunk - d * rf.n;
+  const unsigned head = rf.by_tile ? m : d, l = (head * rf.r_heads) >> 20;
+  part = (int)((b >> 3) - eight * rf.parts);
+  tile = (int)(rf.by_tile ? d : m);
+  kvh = (int)(head - l * (unsigned)g.n_kv_heads);
+  layer = (int)l;
+  return tile < n_tiles && layer < g.n_layers;
+}
+
 // ---- pass A: softmax statistics ----------------------------------------------------------
-template <bool F32, int D, int NBM, int RG>
+// ROW: the grid's row form, several workgroups sharing a chunk, each with its own rows (a template
+// parameter, as the plain form is 0.3-0.7 us slower with the test in it)
+template <bool F32, int D, int NBM, int RG, bool ROW>
 __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_kernel(Geom g, SeqTab tab, AllocIO aio,
                                                           int n_alloc_blocks, int alloc_bpp, int alloc_spread,
-                                                          int n_tiles, const char* q,
+                                                          RowForm rf, const char* q,
                                                           const char* k, float* lpart,
                                                           int rows_padded) {
   using T = Tile<F32, D, RG>;
@@ -212,21 +245,13 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_ke
       alloc_phase_a(aio, blockIdx.x / alloc_bpp, blockIdx.x % alloc_bpp);
     return;
   }
-  // Several workgroups may share a chunk, each with its own rows: chunks of all heads in one row of
-  // the grid, numbered so that those of a chunk are eight apart, next to each other on one XCD, and
-  // the chunks of the smallest call still reach every XCD.
   int tile_no = blockIdx.x - n_alloc_blocks, part = 0, kvh = blockIdx.y, layer = blockIdx.z;
-  if (g.row_parts > 1) {
-    part = (tile_no >> 3) % g.row_parts;
-    const int chunk = (tile_no >> 3) / g.row_parts * 8 + (tile_no & 7), head = chunk / n_tiles;
-    if (head >= g.n_kv_heads * g.n_layers) {      // (padding to whole eights; it may hold a knot)
+  if constexpr (ROW) {
+    if (!row_chunk(g, rf, tab.tile0[tab.n_seqs], tile_no, tile_no, part, kvh, layer)) {    // (it may hold a knot)
       const int64_t item = spread_item(aio, alloc_spread, n_alloc_blocks);
       if (item >= 0) alloc_knot_finish(aio, item, alloc_knot_load(aio, item));
       return;
     }
-    tile_no = chunk % n_tiles;
-    kvh = head % g.n_kv_heads;
-    layer = head / g.n_kv_heads;
   }
   int seq, ch;
   find_tile(tab, tile_no, seq, ch);
@@ -236,10 +261,11 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_ke
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
   constexpr int n_kt = T::kWaveCols;
   const int kt = wave % n_kt, rg = wave / n_kt;
-  const int part_blk0 = part * RG * g.part_blocks;            // this workgroup's first row block
-  const int blk0 = part_blk0 + rg * g.part_blocks;
+  const int part_blocks = ROW ? g.part_blocks : g.blocks_per_group;
+  const int part_blk0 = ROW ? part * RG * part_blocks : 0;  // this workgroup's first row block
+  const int blk0 = part_blk0 + rg * part_blocks;
   int nb_count = g.row_blocks - blk0;
-  nb_count = nb_count < 0 ? 0 : (nb_count > g.part_blocks ? g.part_blocks : nb_count);
+  nb_count = nb_count < 0 ? 0 : (nb_count > part_blocks ? part_blocks : nb_count);
   const float a = g.scale_log2e;
 
   const char* kbase = k + ((int64_t)layer * g.sl + (int64_t)kvh * g.sh + (int64_t)tok0 * g.st) * T::kEsize;
@@ -265,13 +291,13 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_ke
   u32x4 qreg[NBM][T::kHalfU4];
   {
     u32x4 qtmp[QStage<F32, D, NBM>::kLoads];
-    q_fetch<F32, D, NBM, QStage<F32, D, NBM>::kLoads>(qtmp, g, q, layer, kvh, seq, part_blk0, g.part_blocks);
+    q_fetch<F32, D, NBM, QStage<F32, D, NBM>::kLoads>(qtmp, g, q, layer, kvh, seq, part_blk0, part_blocks);
     k_issue<F32, D, RG, T::kLoads>(pre, kbase, ld_off, ld_stride, ld_last);
     // the allocation's knot of this wave: its loads are cold and go out last, so that nothing the
     // workgroup needs first waits behind them; they are consumed once the first tile is in LDS
     if (a_item >= 0) a_ld = alloc_knot_load(aio, a_item);
     for (int grp = 0; grp < RG; ++grp) {
-      if (grp) q_fetch<F32, D, NBM, QStage<F32, D, NBM>::kLoads>(qtmp, g, q, layer, kvh, seq, part_blk0 + grp * g.part_blocks, g.part_blocks);
+      if (grp) q_fetch<F32, D, NBM, QStage<F32, D, NBM>::kLoads>(qtmp, g, q, layer, kvh, seq, part_blk0 + grp * part_blocks, part_blocks);
       if (grp) __syncthreads();
       q_park<F32, D, NBM, QStage<F32, D, NBM>::kLoads>(qtmp, ktile);
       __syncthreads();
@@ -307,8 +333,8 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_ke
     }
     __syncthreads();
     // merge the key subtiles of every row group
-    for (int r = 32 * part_blk0 + threadIdx.x; r < min(rows_padded, 32 * (part_blk0 + RG * g.part_blocks)); r += 256) {
-      const int blk = (r >> 5) - part_blk0, grp = blk / g.part_blocks, nb = blk - grp * g.part_blocks;
+    for (int r = 32 * part_blk0 + threadIdx.x; r < (ROW ? min(rows_padded, 32 * (part_blk0 + RG * part_blocks)) : rows_padded); r += 256) {
+      const int blk = (r >> 5) - part_blk0, grp = blk / part_blocks, nb = blk - grp * part_blocks;
       float mm = -INFINITY, zz = 0.f;
       for (int t = 0; t < n_kt; ++t) {
         const float2 st = wstat[grp * n_kt + t][nb][r & 31];
@@ -382,10 +408,11 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_stats_ke
 }
 
 // ---- pass B: normalised window sums ------------------------------------------------------
-template <bool F32, int D, int NBM, int RG>
+// ROW: the grid's row form, several workgroups sharing a chunk, each with a piece of its keys
+template <bool F32, int D, int NBM, int RG, bool ROW>
 __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_accum_kernel(Geom g, SeqTab tab, AllocIO aio,
                                                           int n_alloc_blocks, int alloc_bpp, int alloc_spread,
-                                                          const char* q,
+                                                          RowForm rf, const char* q,
                                                           const char* k, const float* lpart,
                                                           const float* lse,
                                                           float* raw, float2* range, int max_chunks,
@@ -405,9 +432,12 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_accum_ke
       alloc_phase_a(aio, blockIdx.x / alloc_bpp, blockIdx.x % alloc_bpp);
     return;
   }
+  int tile_no = blockIdx.x - n_alloc_blocks, piece = 0, kvh = blockIdx.y, layer = blockIdx.z;
+  bool live = true;
+  if constexpr (ROW) live = row_chunk(g, rf, tab.tile0[tab.n_seqs], tile_no, tile_no, piece, kvh, layer);
   int seq, ch;
-  find_tile(tab, blockIdx.x - n_alloc_blocks, seq, ch);
-  const int kvh = blockIdx.y, layer = blockIdx.z;
+  find_tile(tab, tile_no, seq, ch);
+  if constexpr (ROW) ch = ch * g.accum_parts + piece;
   const int tok0 = tab.cu[seq], L = tab.cu[seq + 1] - tok0, P = L - g.window;
   const int hi = (seq * g.n_layers + layer) * g.n_kv_heads + kvh;
   // (the wave index is uniform over a wave: saying so keeps what derives from it in scalar registers)
@@ -425,6 +455,8 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_accum_ke
   // spread form of the allocation's first phase (only when no statistics kernel carries it)
   const int64_t a_item = spread_item(aio, alloc_spread, n_alloc_blocks);
   if (a_item >= 0) alloc_knot_finish(aio, a_item, alloc_knot_load(aio, a_item));
+  if constexpr (ROW)
+    if (!live || j_begin >= P) return;      // (padding, or a piece of window positions alone)
   // byte offsets inside one head's keys fit 32 bits (checked on the host)
   const unsigned tok_bytes = (unsigned)(g.st * T::kEsize);
   const int ld_row0 = T::kPrivate ? 32 * (int)(threadIdx.x >> 6) + (int)(threadIdx.x & 63) / T::kRowU4
@@ -612,9 +644,8 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_accum_ke
       vmax = fmaxf(vmax, val);
     }
   }
-  // Value range of the chunk: the selection scales its first radix digit to the range of the head's
-  // metric.
-  if (RG > 1) __syncthreads();   // (colred: the last tile's sums have been read)
+  // Value range of the chunk, one entry per wave (neutral where a wave wrote nothing): the selection
+  // scales its first radix digit to the range of the head's metric.
 #pragma unroll
   for (int o = 16; o > 0; o >>= 1) {
     vmin = fminf(vmin, __shfl_xor(vmin, o));
@@ -622,15 +653,21 @@ __global__ __launch_bounds__(256, (F32 && D == 128) ? 1 : 2) void score_accum_ke
   }
   int ln0;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln0));
-  if (ln0 == 0) {
-    colred[wave][0] = vmin;
-    colred[wave][1] = vmax;
+  if (!ROW || g.accum_parts == 1) {
+    if (ln0 == 0) range[((int64_t)hi * max_chunks + ch) * 4 + wave] = make_float2(vmin, vmax);
+  } else {
+    // one entry per piece, so that the pieces of a chunk take no more room (two barriers: 0.1-0.5 us)
+    if (RG > 1) __syncthreads();   // (colred: the last tile's sums have been read)
+    if (ln0 == 0) {
+      colred[wave][0] = vmin;
+      colred[wave][1] = vmax;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      range[(int64_t)hi * max_chunks + ch] =
+          make_float2(fminf(fminf(colred[0][0], colred[1][0]), fminf(colred[2][0], colred[3][0])),
+                      fmaxf(fmaxf(colred[0][1], colred[1][1]), fmaxf(colred[2][1], colred[3][1])));
   }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    range[(int64_t)hi * max_chunks + ch] =
-        make_float2(fminf(fminf(colred[0][0], colred[1][0]), fminf(colred[2][0], colred[3][0])),
-                    fmaxf(fmaxf(colred[0][1], colred[1][1]), fmaxf(colred[2][1], colred[3][1])));
 }
 
 // ---- pooling + forced positions (stand-alone scores) -------------------------------------
@@ -661,42 +698,49 @@ static int launch_raw_t(const HostCfg& hc, const WsLayout& lay, const void* q, c
   float* raw = reinterpret_cast<float*>(ws + lay.raw);
   float2* range = reinterpret_cast<float2*>(ws + lay.range);
   const SeqTab tabA = tiles_for(hc.seq, g.chunk_keys, 0);
-  const SeqTab tabB = tiles_for(hc.seq, g.accum_keys, g.window);
-  const int tilesA = tabA.tile0[tabA.n_seqs];
-  const int64_t chunksA = (int64_t)tilesA * g.n_kv_heads * g.n_layers;
-  const int64_t wgsA = g.row_parts > 1 ? (chunksA + 7) / 8 * 8 * g.row_parts : chunksA;
+  const int tilesA = tabA.tile0[tabA.n_seqs], n_heads = g.n_kv_heads * g.n_layers;
+  const int64_t chunksA = (int64_t)tilesA * n_heads;
+  const int64_t eights = (chunksA + 7) / 8 * 8;
   AllocIO io;
   memset(&io, 0, sizeof(io));
   // The allocation never looks at scores, so its first phase (hull vertices) rides in the score
   // kernels: spread over the prologues of the statistics kernel's workgroups, one knot per wave,
-  // when there are enough of them; else a few extra workgroups at the front of its grid.  Without
+  // when there are enough of them (counted in chunks: in calls that cut chunks up it is the shorter way
+  // to leave it to workgroups of its own); else a few extra workgroups at the front of its grid.  Without
   // a statistics kernel (log-sum-exp supplied) the accumulation kernel carries it the same way.
   // Extra workgroups are padded to a multiple of 8 so that a chunk lands on the same XCD (and its
   // L2) in both passes.
-  const int64_t wgsB = (int64_t)tabB.tile0[tabB.n_seqs] * g.n_kv_heads * g.n_layers;
-  int frontA = 0, bppA = 1, spreadA = 0, frontB = 0, bppB = 1, spreadB = 0;
+  int front = 0, bpp = 1;
+  bool spread = false;
+  int64_t n_knots = 0;
   if (aio) {
     io = *aio;
-    const int64_t n_knots = (int64_t)aio->n_problems * aio->n_heads * aio->n_grid;
-    const int bpp = alloc_blocks_a(aio->n_heads, aio->n_grid);
-    if (!lse) {
-      spreadA = alloc_spread_knots(n_knots, wgsA);
-      if (!spreadA) { bppA = bpp; frontA = (aio->n_problems * bpp + 7) / 8 * 8; }
-    } else {
-      spreadB = alloc_spread_knots(n_knots, wgsB);
-      if (!spreadB) { bppB = bpp; frontB = (aio->n_problems * bpp + 7) / 8 * 8; }
-    }
+    n_knots = (int64_t)aio->n_problems * aio->n_heads * aio->n_grid;
+    spread = alloc_spread_knots(n_knots, chunksA) > 0;
+    if (!spread) { bpp = alloc_blocks_a(aio->n_heads, aio->n_grid); front = (aio->n_problems * bpp + 7) / 8 * 8; }
   }
-  const dim3 gridA = g.row_parts > 1 ? dim3((unsigned)wgsA + frontA) : dim3(tilesA + frontA, g.n_kv_heads, g.n_layers);
-  dim3 gridB(tabB.tile0[tabB.n_seqs] + frontB, g.n_kv_heads, g.n_layers);
+  // The statistics kernel in row form where the configuration asks for it; the accumulation kernel
+  // where chunks are cut up, and where a plain grid would repeat the extra workgroups for every head.
+  const bool rowA = g.row_parts > 0;
+  const int frontA = lse ? 0 : front, frontB = lse ? front : 0;
+  const bool rowB = g.accum_parts > 1 || (frontB > 0 && n_heads > 1 && chunksA <= kRowChunks);
+  const SeqTab tabB = rowB ? tabA : tiles_for(hc.seq, g.accum_keys, g.window);
+  const int tilesB = tabB.tile0[tabB.n_seqs];
+  const int64_t wgsA = rowA ? eights * g.row_parts : chunksA;
+  const int64_t wgsB = rowB ? eights * g.accum_parts : (int64_t)tilesB * n_heads;
+  const dim3 gridA = rowA ? dim3((unsigned)wgsA + frontA) : dim3(tilesA + frontA, g.n_kv_heads, g.n_layers);
+  const dim3 gridB = rowB ? dim3((unsigned)wgsB + frontB) : dim3(tilesB + frontB, g.n_kv_heads, g.n_layers);
   if (!lse) {
-    auto* stats = g.row_parts > 1 ? score_stats_kernel<F32, D, 1, RG> : score_stats_kernel<F32, D, NBM, RG>;
-    launch_staged(kStStats, stats, gridA, dim3(256), st, g, tabA, io, frontA, bppA, spreadA, tilesA, (const char*)q,
-                  (const char*)k, lpart, lay.rows_padded);
+    auto* stats = rowA ? score_stats_kernel<F32, D, 1, RG, true> : score_stats_kernel<F32, D, NBM, RG, false>;
+    launch_staged(kStStats, stats, gridA, dim3(256), st, g, tabA, io, frontA, bpp,
+                  spread ? alloc_spread_knots(n_knots, wgsA) : 0, row_form(g, rowA ? g.row_parts : 1, tilesA, rowB),
+                  (const char*)q, (const char*)k, lpart, lay.rows_padded);
   }
-  launch_staged(kStAccum, score_accum_kernel<F32, D, NBM, RG>, gridB, dim3(256), st, g, tabB, io,
-                frontB, bppB, spreadB, (const char*)q, (const char*)k, (const float*)lpart, lse, raw,
-                range, lay.max_chunks, lay.rows_padded);
+  auto* accum = rowB ? score_accum_kernel<F32, D, NBM, RG, true> : score_accum_kernel<F32, D, NBM, RG, false>;
+  launch_staged(kStAccum, accum, gridB, dim3(256), st, g, tabB, io, frontB, bpp,
+                spread && lse ? alloc_spread_knots(n_knots, wgsB) : 0,
+                row_form(g, g.accum_parts, tilesB, rowA || lse), (const char*)q, (const char*)k, (const float*)lpart, lse,
+                raw, range, lay.max_chunks, lay.rows_padded);
   return check_launch();
 }
 

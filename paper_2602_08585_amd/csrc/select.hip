@@ -63,7 +63,8 @@ __device__ __forceinline__ unsigned hist_add(unsigned* lh, unsigned bin, bool ac
 struct SelGeom {
   int32_t n_layers, n_kv_heads, total_tokens, max_slices;
   int32_t window, pool_kernel, n_sink;
-  int32_t range_chunk;    // positions covered by one range entry
+  int32_t range_chunk;    // positions covered by one group of range entries
+  int32_t range_per;      // entries per group
   int32_t range_tail;     // trailing positions without entries (the window, fused path)
   int32_t range_stride;   // entries per head in the range array
   int32_t slices_per_wg;  // slices one workgroup of sel_hist takes
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(1024) void sel_hist_kernel(SelGeom sg, SeqTab tab, 
   // range of the head's metric: every workgroup of the head folds the same entries
   float mn = INFINITY, mx = -INFINITY;
   {
-    const int n_ent = (L - sg.range_tail + sg.range_chunk - 1) / sg.range_chunk;
+    const int n_ent = (L - sg.range_tail + sg.range_chunk - 1) / sg.range_chunk * sg.range_per;
     const float2* rp = range + (int64_t)hi * sg.range_stride;
     if ((t & ~63) < n_ent) {
       for (int e = t; e < n_ent; e += 1024) {
@@ -1002,8 +1003,8 @@ int launch_select_compact(const HostCfg& hc, const WsLayout& lay, const AllocIO*
   const SeqTab tabH = tiles_for(hc.seq, kSliceElems, 0);
   SelGeom sg{g.n_layers, g.n_kv_heads, g.total_tokens, lay.max_slices,
              g.window, g.pool_kernel, g.n_sink,
-             pool ? g.accum_keys : kSliceElems, pool ? g.window : 0,
-             pool ? lay.max_chunks : lay.max_slices, 1};
+             pool ? g.accum_keys : kSliceElems, pool ? range_per(g) : 1, pool ? g.window : 0,
+             pool ? lay.max_chunks * range_per(g) : lay.max_slices, 1};
   if (select_whole_head(hc)) {
     // two kernels: one workgroup per head decides, then the gather
     unsigned* keepmask = reinterpret_cast<unsigned*>(ws + lay.keepmask);
