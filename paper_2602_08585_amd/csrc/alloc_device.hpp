@@ -198,8 +198,8 @@ __host__ __device__ inline int alloc_spread_knots(int64_t n_knots, int64_t n_wgs
 
 // Phase B, general form, for problem p (after phase A's flags are visible): any number of heads,
 // segments and units; lds: 4 KiB of scratch.  Everything is walked in the workspace and in global
-// memory, the radix select of the threshold gain is wave 0's alone (8-bit digits).  For the
-// problems that neither form below takes.
+// memory, the radix select of the threshold gain is wave 0's alone (8-bit digits).  For problems
+// of more than 1024 heads or 65536 knots, which neither form below takes.
 __device__ inline void alloc_phase_b_generic(const AllocIO& io, int p, long long B, char* lds) {
   const int NH = io.n_heads, Gp = io.n_grid, t = threadIdx.x, nt = blockDim.x;
   const int lane = t & 63, wave = t >> 6;
@@ -276,6 +276,7 @@ __device__ inline void alloc_phase_b_generic(const AllocIO& io, int p, long long
       for (int k = 0; k < 4; ++k) hist[4 * lane + k] = 0ull;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
       for (int64_t i = lane; i < nseg; i += 64) {
         const unsigned w = sw[i];
         if (w) {
@@ -343,12 +344,15 @@ __device__ inline void alloc_phase_b_generic(const AllocIO& io, int p, long long
   if (t == 0) io.status[p] = infeasible ? LUKV_ST_INFEASIBLE : 0;
 }
 
-constexpr int kAllocLdsBytes = 41472;     // LDS the 1024-thread forms of phase B need
+// LDS of the 1024-thread forms of phase B: the small form, and the list form with its summary behind it
+constexpr int kAllocSmallLds = 25152;
+constexpr int kAllocListLds = 24728;
+constexpr int kAllocLdsBytes = 25152 + 64;
 constexpr int kAllocListSegs = 65536;     // most knots of a problem that the list form takes
 constexpr int kAllocListHeads = 1024;     // and most heads
 
 // Phase B, list form (problems of up to 1024 heads and 65536 knots, by a workgroup of 1024 threads
-// with kAllocLdsBytes of LDS), in two steps so that several budgets can be solved for from one list.
+// with kAllocListLds of LDS), in two steps so that several budgets can be solved for from one list.
 //   alloc_list_prep   the hull segments that still offer units, as a list in the workspace (gain key,
 //                     units, head), in no particular order: everything after it is integer sums.
 //   alloc_list_solve  weighted radix select of the threshold gain over the list, then per-head sums.
@@ -356,8 +360,8 @@ constexpr int kAllocListHeads = 1024;     // and most heads
 // vertex flags become bit masks by ballots over consecutive knots (a head's last knot is always a
 // vertex, so the next set bit never belongs to another head), only live segments - a fifth of the
 // knots or fewer - divide and are walked again, and up to 4096 of them stay in registers for the
-// digits.  One problem of 256 heads x 64 knots: 82 us with every knot walked in the workspace for
-// every digit, 49 us this way.
+// digits.  A call with 256 heads x 64 knots: 50 us with every knot walked in the workspace for every
+// digit, 36 us this way.
 struct AllocListHead {
   long long sum_min, offer;               // minimum retention, units on offer
   unsigned long long and_keys, or_keys;   // over the live keys
@@ -365,14 +369,20 @@ struct AllocListHead {
   unsigned pad[6];
 };
 static_assert(sizeof(AllocListHead) == 64, "one cache line per problem");
+static_assert(kAllocSmallLds <= kAllocLdsBytes && kAllocListLds <= kAllocLdsBytes - (int)sizeof(AllocListHead),
+              "the forms fit, the list form beside its summary");
+
+// Up to 1024 knots a thread has one at most, and its segment stays in registers: no list (100 heads x 10
+// knots, a call: 13.8 us by way of the list, 12.3 without).
+struct AllocOwn { unsigned long long key; unsigned w; int h; };
 
 __host__ __device__ inline bool alloc_list_ok(int n_heads, int n_grid) {
   return n_heads <= kAllocListHeads && (int64_t)n_heads * n_grid <= kAllocListSegs;
 }
 
-// The list of problem p; *head (LDS) holds its summary after the next barrier.  False (and no list,
-// the flags intact) if the units on offer don't fit 31 bits.
-__device__ inline bool alloc_list_prep(const AllocIO& io, int p, char* lds, AllocListHead* head) {
+// The list of problem p (OWN: this thread's segment); *head (LDS) holds its summary after the next barrier.
+template <bool OWN>
+__device__ inline void alloc_list_prep(const AllocIO& io, int p, char* lds, AllocListHead* head, AllocOwn* own) {
   const int NH = io.n_heads, Gp = io.n_grid, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t hbase = (int64_t)p * NH, sbase = hbase * Gp;
   const int nseg = NH * Gp;
@@ -424,8 +434,6 @@ __device__ inline bool alloc_list_prep(const AllocIO& io, int p, char* lds, Allo
       if (any_bad) atomicOr(&head->bad, 1u);
     }
   }
-  __syncthreads();
-  if (head->offer >= (1ll << 31)) return false;
   // Vertices of four words (256 knots) per wave and round: one segment per vertex, to the next one,
   // clipped to (b_min, cap]; the live ones go to the list (over the vertex flags and the segment
   // arrays, which nothing else reads any more).
@@ -465,6 +473,15 @@ __device__ inline bool alloc_list_prep(const AllocIO& io, int p, char* lds, Allo
         w = hi > lo ? (unsigned)hi - (unsigned)lo : 0u;
         key = gain_key(((double)ub[u] - (double)ua[u]) / (double)((long long)nb[u] - na[u]));
       }
+      if constexpr (OWN) {
+        if (w) {
+          *own = AllocOwn{key, w, h};
+          k_and &= key;
+          k_or |= key;
+          any_w = true;
+        }
+        continue;
+      }
       const unsigned long long live = __ballot(w != 0u);
       if (live) {
         unsigned at = 0;
@@ -492,25 +509,35 @@ __device__ inline bool alloc_list_prep(const AllocIO& io, int p, char* lds, Allo
       atomicOr(&head->or_keys, ((unsigned long long)o_hi << 32) | o_lo);
     }
   }
-  return true;
 }
 
-// Budgets of problem p for B units, from its list.  head: LDS, complete (a barrier after its writer).
-__device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, const AllocListHead* head, char* lds) {
-  constexpr int kReg = 4;                 // segments a thread keeps in registers
+// Sums over the workgroup's threads before this one, of 32-bit or 64-bit counts; part has 16 slots.
+__device__ __forceinline__ unsigned alloc_scan(unsigned v, void* part) { return block_scan_u32(v, static_cast<unsigned*>(part)); }
+__device__ __forceinline__ unsigned long long alloc_scan(unsigned long long v, void* part) {
+  long long total;
+  return (unsigned long long)block_scan_i64((long long)v, static_cast<long long*>(part), &total);
+}
+
+// Budgets of problem p for B units, from its list (OWN: from every thread's segment).  head: LDS, complete (a barrier after its writer).
+// W holds counts of units: 32 bits while the units on offer fit 31, else 64.
+template <class W, bool OWN>
+__device__ inline void alloc_list_solve_as(const AllocIO& io, int p, long long B, const AllocListHead* head, char* lds,
+                                           const AllocOwn& own) {
+  constexpr int kReg = OWN ? 1 : 4;       // segments a thread keeps in registers
   const int NH = io.n_heads, t = threadIdx.x;
   const int64_t hbase = (int64_t)p * NH, sbase = hbase * io.n_grid;
-  unsigned* bh = reinterpret_cast<unsigned*>(lds);                                   // units per bin
-  unsigned* bc = bh + kHistBins;                                                     // segments per bin
-  unsigned* h_gt = reinterpret_cast<unsigned*>(lds + 16384);                         // per-head sums
-  unsigned* h_eq = h_gt + 1024;
-  unsigned* spart = reinterpret_cast<unsigned*>(lds + 24576);                        // 16 slots
-  unsigned* pick = spart + 16;                                                       // bin, units still wanted
-  unsigned long long* sel = reinterpret_cast<unsigned long long*>(lds + 24704);      // g*
+  W* bh = reinterpret_cast<W*>(lds);                                                 // units per bin
+  unsigned* bc = reinterpret_cast<unsigned*>(lds + kHistBins * sizeof(W));           // segments per bin
+  W* h_gt = bh;                                                                      // per-head sums (after the bins)
+  W* h_eq = bh + 1024;
+  void* spart = lds + 24576;                                                         // 16 slots
+  W* pick = reinterpret_cast<W*>(lds + 24704);                                       // bin, units still wanted
+  unsigned long long* sel = reinterpret_cast<unsigned long long*>(lds + 24720);      // g* -> 24728
+  static_assert(kHistBins * (sizeof(unsigned long long) + 4) <= 24576, "bins below the scan's slots");
   const long long R = B - head->sum_min;
   const bool infeasible = head->bad != 0 || R < 0 || R > head->offer;
   const bool active = !infeasible && R > 0;
-  const int n = active ? (int)head->n_live : 0;
+  const int n = active && !OWN ? (int)head->n_live : 0;
   const int lb = t < NH ? io.b_min[hbase + t] : 0;
   const unsigned long long* gk = io.seg_key + sbase;
   const unsigned* gw = io.seg_w + sbase;
@@ -520,8 +547,8 @@ __device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, c
 #pragma unroll
   for (int u = 0; u < kReg; ++u) {
     const int i = t + 1024 * u;
-    rk[u] = i < n ? gk[i] : 0ull;
-    rw[u] = i < n ? gw[i] : 0u;
+    rk[u] = OWN ? own.key : i < n ? gk[i] : 0ull;
+    rw[u] = OWN ? (active ? own.w : 0u) : i < n ? gw[i] : 0u;
   }
   auto each = [&](auto f) {               // every segment of this thread: (index, key, units > 0)
 #pragma unroll
@@ -530,12 +557,12 @@ __device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, c
 #pragma unroll 4
     for (int i = t + 1024 * kReg; i < n; i += 1024) f(i, gk[i], gw[i]);
   };
+  auto head_of = [&](int i) { return OWN ? own.h : gh[i]; };
   const unsigned long long differ = head->and_keys ^ head->or_keys;
   int rest = active && differ ? 64 - __clzll((long long)differ) : 0;     // low bits still open
   unsigned long long prefix = rest == 64 ? 0ull : head->and_keys & ~((1ull << rest) - 1ull);
-  unsigned want = (unsigned)R;            // (the list form is for totals below 2^31)
+  W want = (W)R;
   __syncthreads();
-  if (t < 1024) { h_gt[t] = 0u; h_eq[t] = 0u; }
   if (t == 0) *sel = 0ull;
   bool single = false;
   while (rest > 0) {
@@ -543,23 +570,23 @@ __device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, c
     const unsigned mask = (1u << (rest - sh)) - 1u;
     const unsigned long long hi_mask = rest == 64 ? 0ull : ~((1ull << rest) - 1ull);
     __syncthreads();
-    bh[t] = 0u; bh[t + 1024] = 0u;
+    bh[t] = 0; bh[t + 1024] = 0;
     bc[t] = 0u; bc[t + 1024] = 0u;
     __syncthreads();
     each([&](int, unsigned long long key, unsigned w) {
       if ((key & hi_mask) == (prefix & hi_mask)) {
         const unsigned d = (unsigned)(key >> sh) & mask;
-        atomicAdd(&bh[d], w);
+        atomicAdd(&bh[d], (W)w);
         atomicAdd(&bc[d], 1u);
       }
     });
     __syncthreads();
-    const unsigned a1 = bh[2047 - 2 * t], a0 = bh[2046 - 2 * t];
-    const unsigned before = block_scan_u32(a1 + a0, spart);
-    if (before < want && want <= before + a1) { pick[0] = 2047 - 2 * t; pick[1] = want - before; }
-    else if (before + a1 < want && want <= before + a1 + a0) { pick[0] = 2046 - 2 * t; pick[1] = want - before - a1; }
+    const W a1 = bh[2047 - 2 * t], a0 = bh[2046 - 2 * t];
+    const W before = alloc_scan((W)(a1 + a0), spart);
+    if (before < want && want <= before + a1) { pick[0] = (W)(2047 - 2 * t); pick[1] = want - before; }
+    else if (before + a1 < want && want <= before + a1 + a0) { pick[0] = (W)(2046 - 2 * t); pick[1] = want - before - a1; }
     __syncthreads();
-    const unsigned bin = pick[0];
+    const unsigned bin = (unsigned)pick[0];
     want = pick[1];
     prefix |= (unsigned long long)bin << sh;
     rest = sh;
@@ -574,25 +601,35 @@ __device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, c
   }
   if (!single && t == 0) *sel = prefix;
   __syncthreads();
+  h_gt[t] = 0;
+  h_eq[t] = 0;
+  __syncthreads();
   // budgets: everything above g*, the units at exactly g* in head order
   const unsigned long long kstar = *sel;
   each([&](int i, unsigned long long key, unsigned w) {
-    if (key > kstar) atomicAdd(&h_gt[gh[i]], w);
-    else if (key == kstar) atomicAdd(&h_eq[gh[i]], w);
+    if (key > kstar) atomicAdd(&h_gt[head_of(i)], (W)w);
+    else if (key == kstar) atomicAdd(&h_eq[head_of(i)], (W)w);
   });
   __syncthreads();
-  const unsigned gt = t < NH ? h_gt[t] : 0u, eq = t < NH ? h_eq[t] : 0u;
-  const unsigned eq_before = block_scan_u32(eq, spart);
+  const W gt = t < NH ? h_gt[t] : 0, eq = t < NH ? h_eq[t] : 0;
+  const W eq_before = alloc_scan(eq, spart);
   if (t < NH) {
-    unsigned take = active && want > eq_before ? want - eq_before : 0u;
+    W take = active && want > eq_before ? want - eq_before : 0;
     take = take < eq ? take : eq;
-    io.budgets[hbase + t] = (int32_t)(lb + (long long)gt + take);
+    io.budgets[hbase + t] = (int32_t)(lb + (long long)gt + (long long)take);
   }
   if (t == 0) io.status[p] = infeasible ? LUKV_ST_INFEASIBLE : 0;
 }
 
+template <bool OWN = false>
+__device__ inline void alloc_list_solve(const AllocIO& io, int p, long long B, const AllocListHead* head, char* lds,
+                                        const AllocOwn& own = AllocOwn{}) {
+  if (head->offer < (1ll << 31)) alloc_list_solve_as<unsigned, OWN>(io, p, B, head, lds, own);
+  else alloc_list_solve_as<unsigned long long, OWN>(io, p, B, head, lds, own);
+}
+
 // Phase B for a small problem (at most 1024 knots and 64 heads) by a workgroup of 1024 threads
-// with 32 KiB of LDS: one thread per knot; the hull segments that still offer units are compacted
+// with kAllocSmallLds of LDS: one thread per knot; the hull segments that still offer units are compacted
 // into a list, and the threshold gain is found by ranking every such segment against all others
 // (a few hundred at most), which needs no digit passes.  Same result as the other forms.
 // What a thread of alloc_phase_b_small reads from global memory, so that a caller can issue the
@@ -767,11 +804,17 @@ __device__ inline void alloc_phase_b(const AllocIO& io, int p, char* lds) {
   }
   if (alloc_list_ok(io.n_heads, io.n_grid)) {
     AllocListHead* head = reinterpret_cast<AllocListHead*>(lds + kAllocLdsBytes - sizeof(AllocListHead));
-    if (alloc_list_prep(io, p, lds, head)) {
+    if (io.n_heads * io.n_grid <= 1024) {
+      AllocOwn own{0ull, 0u, 0};
+      alloc_list_prep<true>(io, p, lds, head, &own);
       __syncthreads();
-      alloc_list_solve(io, p, io.B[p], head, lds);
-      return;
+      alloc_list_solve<true>(io, p, io.B[p], head, lds, own);
+    } else {
+      alloc_list_prep<false>(io, p, lds, head, nullptr);
+      __syncthreads();
+      alloc_list_solve<false>(io, p, io.B[p], head, lds);
     }
+    return;
   }
   alloc_phase_b_generic(io, p, io.B[p], lds);
 }

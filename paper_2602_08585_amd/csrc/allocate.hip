@@ -37,7 +37,7 @@ struct RhoBatch { int64_t B[kRhoBatch]; };
 __global__ __launch_bounds__(1024) void allocate_list_kernel(AllocIO io, AllocListHead* heads) {
   __shared__ __align__(16) char lds[kAllocLdsBytes];
   __shared__ AllocListHead head;
-  alloc_list_prep(io, blockIdx.x, lds, &head);
+  alloc_list_prep<false>(io, blockIdx.x, lds, &head, nullptr);
   __syncthreads();
   if (threadIdx.x == 0) heads[blockIdx.x] = head;
 }
@@ -52,9 +52,7 @@ __global__ __launch_bounds__(1024) void allocate_rho_kernel(AllocIO io, RhoBatch
   if (heads) {
     if (threadIdx.x == 0) head = heads[p];
     __syncthreads();
-    if (head.offer < (1ll << 31)) alloc_list_solve(io, p, rb.B[r], &head, lds);
-    // (no list was made; the ratios of a problem write the same segments over each other)
-    else alloc_phase_b_generic(io, p, rb.B[r], lds);
+    alloc_list_solve(io, p, rb.B[r], &head, lds);
   } else {
     alloc_phase_b_small(io, p, rb.B[r], lds, alloc_small_load(io, p), nullptr, true);
   }
