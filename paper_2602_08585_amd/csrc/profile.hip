@@ -6,9 +6,10 @@
 // bins, about one token each for scores of any spread, since float bits are nearly a logarithm);
 // tokens are gathered by bin, and a token's rank is its bin's start plus the tokens of that bin that
 // come before it, by a direct count.  A context that crowds a bin with more than kCrowd tokens (ties,
-// an infinity among ordinary scores) sorts with a bitonic network instead.
-//   2048 contexts of 4000 tokens: 221 us with the network for all (78 steps over LDS with a barrier
-//   each, bound by them and by the compares), 51 us this way; 65 MB take 13 us from memory.
+// an infinity among ordinary scores, scores of both signs) sorts with a bitonic network instead.
+//   2048 contexts of 4000 tokens: 212 us with a network in LDS for all (78 steps), 50 us this way
+//   (65 MB take 13 us from memory); crowded ones 124-146 us, the bins' cost included, where the
+//   network in LDS would take 220-224.
 #include "lukv_internal.hpp"
 
 namespace lukv {
@@ -23,6 +24,47 @@ __device__ __forceinline__ unsigned curve_key(float f) {
 
 constexpr int kCurveBins = 4096;   // bins of the ranking
 constexpr unsigned kCrowd = 48;    // tokens in one bin up to which they are counted directly
+
+// Bitonic network over 4096 keys, thread t holding keys 4t .. 4t+3: steps over distances 1 and 2 are in
+// the thread, up to 128 between lanes of a wave (four of every six by DPP), and only the ten wider ones
+// go through LDS, which is what bounds the network (2 x 8 bytes read and written per pair and step).
+template <int CTRL>
+__device__ __forceinline__ unsigned long long sort_dpp(unsigned long long x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
+}
+
+// value of lane ^ X
+template <int X>
+__device__ __forceinline__ unsigned long long sort_partner(unsigned long long x) {
+  if constexpr (X == 1) return sort_dpp<0xB1>(x);                     // quad_perm [1,0,3,2]
+  else if constexpr (X == 2) return sort_dpp<0x4E>(x);                // quad_perm [2,3,0,1]
+  else if constexpr (X == 4) return sort_dpp<0x1B>(sort_dpp<0x141>(x));   // 7 - i of a half row, then 3 - i of a quad
+  else if constexpr (X == 8) return sort_dpp<0x128>(x);               // rotation of a row by 8
+  else {
+    const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)x, X), hi = (unsigned)__shfl_xor((int)(unsigned)(x >> 32), X);
+    return ((unsigned long long)hi << 32) | lo;
+  }
+}
+
+// what the lower (or upper) place of a pair keeps; down: this run is sorted descending
+__device__ __forceinline__ unsigned long long sort_keep(unsigned long long mine, unsigned long long other, bool lower, bool down) {
+  return (mine > other) == (lower == down) ? mine : other;
+}
+
+__device__ __forceinline__ void sort_pair(unsigned long long& a, unsigned long long& b, bool down) {
+  const unsigned long long x = a, y = b;
+  a = sort_keep(x, y, true, down);
+  b = sort_keep(y, x, false, down);
+}
+
+template <int J>
+__device__ __forceinline__ void sort_lanes(unsigned long long (&v)[4], int t, int k) {
+  const bool lower = ((4 * t) & J) == 0, down = ((4 * t) & k) == 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = sort_keep(v[r], sort_partner<J / 4>(v[r]), lower, down);
+}
 
 __global__ __launch_bounds__(1024) void profile_curves_kernel(const float* importance, const float* scores,
                                                               const int32_t* knots, int T, int n_grid,
@@ -106,28 +148,37 @@ __global__ __launch_bounds__(1024) void profile_curves_kernel(const float* impor
     }
     __syncthreads();
   } else {
-    // padding sorts last
+    // (any order to begin with; padding sorts last)
+    unsigned long long v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) keys[t + 1024 * u] = t + 1024 * u < T ? composite(key[u], t + 1024 * u) : 0ull;
-    __syncthreads();
+    for (int u = 0; u < 4; ++u) v[u] = t + 1024 * u < T ? composite(key[u], t + 1024 * u) : 0ull;
+#pragma unroll 1
     for (int k = 2; k <= kCurveMaxT; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll 1
+      for (int j = k >> 1; j >= 256; j >>= 1) {
 #pragma unroll
-        for (int u = 0; u < kCurveMaxT / 2048; ++u) {
-          const int q = t + 1024 * u;
-          const int i = 2 * q - (q & (j - 1)), l = i + j;
-          const unsigned long long a = keys[i], b = keys[l];
-          const bool down = (i & k) == 0;              // this run is sorted descending
-          if (down ? a < b : a > b) { keys[i] = b; keys[l] = a; }
-        }
+        for (int r = 0; r < 4; ++r) keys[4 * t + r] = v[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = sort_keep(v[r], keys[(4 * t + r) ^ j], ((4 * t) & j) == 0, ((4 * t) & k) == 0);
         __syncthreads();
       }
+      if (k > 128) sort_lanes<128>(v, t, k);
+      if (k > 64) sort_lanes<64>(v, t, k);
+      if (k > 32) sort_lanes<32>(v, t, k);
+      if (k > 16) sort_lanes<16>(v, t, k);
+      if (k > 8) sort_lanes<8>(v, t, k);
+      if (k > 4) sort_lanes<4>(v, t, k);
+      if (k > 2) {
+        sort_pair(v[0], v[2], ((4 * t) & k) == 0);
+        sort_pair(v[1], v[3], ((4 * t) & k) == 0);
+      }
+      sort_pair(v[0], v[1], ((4 * t) & k) == 0);
+      sort_pair(v[2], v[3], ((4 * t + 2) & k) == 0);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int r = t + 1024 * u;
-      if (r < T) by_rank[r] = imp[0xFFFFFFFFu - (unsigned)keys[r]];
-    }
+    for (int r = 0; r < 4; ++r)
+      if (4 * t + r < T) by_rank[4 * t + r] = imp[0xFFFFFFFFu - (unsigned)v[r]];
     __syncthreads();
   }
   // importance along the ranking: four consecutive ranks per thread, fp64

@@ -23,6 +23,11 @@ def _scores(kind, T, rng):
     elif kind == "infinities":
         s[T // 2] = np.inf
         s[T // 3] = -np.inf
+    elif kind == "outlier":                 # all but one crowded into a bin, few of them equal
+        s = 1.0 + rng.random(T) / 1024
+        s[T // 2] = 1e30
+    elif kind == "half_zero":
+        s[rng.random(T) < 0.5] = 0.0
     elif kind == "equal":
         s[:] = 1.0
     elif kind == "distinct_bits":           # every key in its own bin, in both directions
@@ -30,8 +35,9 @@ def _scores(kind, T, rng):
     return np.ascontiguousarray(s, dtype=np.float32)
 
 
-@pytest.mark.parametrize("T", [1, 2, 63, 1024, 1025, 4095, 4096])
-@pytest.mark.parametrize("kind", ["spread", "tie_48", "tie_49", "signed", "infinities", "equal", "distinct_bits"])
+@pytest.mark.parametrize("T", [1, 2, 63, 127, 129, 1024, 1025, 4095, 4096])
+@pytest.mark.parametrize("kind", ["spread", "tie_48", "tie_49", "signed", "infinities", "outlier", "half_zero", "equal",
+                                  "distinct_bits"])
 def test_profile_ranking(T, kind):
     print("case", T, kind, flush=True)
     rng = np.random.default_rng(T)
