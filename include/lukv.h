@@ -243,7 +243,9 @@ int lukv_evict_budgets(const lukv_config* cfg, const void* q_win, const void* k,
  *            n_q_heads / n_kv_heads <= 16
  *   q_dec    device, dtype, contiguous [n_layers][n_q_heads][n_seqs][head_dim]: one query per
  *            sequence and query head
- *   k_packed, v_packed, offsets as written by lukv_evict / lukv_select_compact
+ *   k_packed, v_packed, offsets as written by lukv_evict / lukv_select_compact; the offsets are a
+ *            prefix sum of row counts (where they fall nonetheless, nothing is read or written out of
+ *            the heads' ranges, heads without rows are zeros, and `out` of the others is unspecified)
  *   out      device float32, contiguous [n_layers][n_q_heads][n_seqs][head_dim]
  *   ws       lukv_decode_workspace_bytes(cfg) bytes, 256-byte aligned. */
 int lukv_decode_workspace_bytes(const lukv_config* cfg, int64_t* bytes);

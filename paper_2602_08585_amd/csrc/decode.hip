@@ -217,6 +217,8 @@ __global__ __launch_bounds__(64 * kDecWaves, NG <= 4 ? (!F32 ? 4 : D == 64 ? 3 :
     const int64_t o0 = NH <= 63 ? lane_i64(probe, hi) : offsets[hi];
     const int64_t o1 = NH <= 63 ? lane_i64(probe, hi + 1) : offsets[hi + 1];
     const int64_t b0 = (o0 >> T::kShift) - sh.first + hi, b1 = (o1 >> T::kShift) - sh.first + hi + 1;
+    // (offsets that fall somewhere have no such numbering: nothing is read or written out of range then)
+    if ((int64_t)f < b0 || (int64_t)f >= b1) continue;
     const unsigned fe = (unsigned)min((int64_t)f_end, b1);
     // rows of this head that this workgroup takes; this wave's steps start at r0, R apart (a head's
     // bytes fit 32 bits: at most 2^20 rows of 512 bytes)
@@ -389,7 +391,8 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecGeom g, const int
     return;
   }
   const unsigned b0 = (unsigned)((o0 >> SHIFT) - sh.first + hi), b1 = (unsigned)((o1 >> SHIFT) - sh.first + hi);
-  const int w0 = (int)(b0 / sh.per), n_part = (int)(b1 / sh.per) - w0 + 1;
+  const unsigned last = (unsigned)g.n_wgs - 1u;          // (no limit but where offsets fall)
+  const int w0 = (int)min(b0 / sh.per, last), n_part = (int)min(b1 / sh.per, last) - w0 + 1;
   const float* hp = part + (((int64_t)w0 + hi) * G + gq) * (D + 2);
   const int64_t bstride = (int64_t)G * (D + 2);
   float m_run = -INFINITY, a = 0.f, l = 0.f;
