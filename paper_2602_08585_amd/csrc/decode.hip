@@ -22,7 +22,9 @@
 //     15.9 / 398 us  one workgroup per 128 rows of the longest possible head (4 of 5 to 12 of 13 of
 //                    them empty), a partial result per block, dot products and a butterfly per row
 //     17.6 / 265 us  equal shares
-//     13.2 / 257 us  and the logits on the matrix cores (5.6 TB/s on the larger)
+//     13.6 / 257 us  and the logits on the matrix cores
+//     13.6 / 234 us  and the larger streamed
+//     12.9 / 225 us  and 512 workgroups, shares at most a block apart (6.4 TB/s on the larger)
 #include <type_traits>
 
 #include "lukv_internal.hpp"
@@ -35,13 +37,16 @@ constexpr int kDecWaves = 4;       // waves of a workgroup of decode_partial (th
 constexpr int64_t kDecStreamBytes = 256ll << 20;   // bytes of K and V from which they are streamed
 
 struct DecGeom {
-  int32_t n_layers, n_q_heads, n_kv_heads, group, n_seqs, n_heads_total, n_wgs;
+  int32_t n_layers, n_q_heads, n_kv_heads, group, n_seqs, n_heads_total, wgs_shift;   // (1 << wgs_shift workgroups)
   float scale_log2e;
 };
 
-// Workgroups resident at once: 4 per CU with four query heads in registers (16-bit rows), 2 with eight.
-// Two rounds of them, so that a few hundred blocks still make one-block shares.
-constexpr int dec_wgs(int ng) { return ng <= 4 ? 2048 : 1024; }
+// Workgroups: two per CU, which every form has resident at once (16-bit rows and four query heads: four).
+// More of them leave more partial results and, where the rest does not fit, a second round: 105 000 rows
+// of 8 heads 20.5 us with 2048, 17.2 with 512 (bf16, d 128, G 4), in float32 35.4 and 27.7 (one workgroup
+// per 128 rows: 23.2 and 30.9).  More heads than that are short ones, most often, and a workgroup meets
+// several, one after the other: 4096 heads of 90 rows 42.9 us with 512, 37.0 with 2048.
+static int dec_wgs_shift(const HostCfg& hc) { return hc.n_hi <= 512 ? 9 : hc.g.group <= 4 ? 11 : 10; }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -93,16 +98,27 @@ struct DecTile {
   static_assert((1 << kShift) == kRows, "rows per block is a power of two");
 };
 
-// Block numbers of all heads (from `first`, the first head's, on) and the share of one workgroup.
-struct DecShare { int64_t first; unsigned total, per; };
+// Block numbers of all heads, from `first`, the first head's, on.  Workgroup w takes the blocks from
+// w * total >> shift on (all shares equal or one apart), or block w if there are no more than workgroups.
+struct DecShare { int64_t first; unsigned total; };
 
 template <int SHIFT>
 __device__ __forceinline__ DecShare dec_share(const DecGeom& g, int64_t off_first, int64_t off_last) {
   DecShare s;
   s.first = off_first >> SHIFT;
   s.total = (unsigned)((off_last >> SHIFT) - s.first + g.n_heads_total);
-  s.per = (s.total + (unsigned)g.n_wgs - 1u) / (unsigned)g.n_wgs;
   return s;
+}
+
+__device__ __forceinline__ unsigned share_begin(unsigned w, unsigned total, int shift) {
+  return total <= (1u << shift) ? min(w, total) : (unsigned)((uint64_t)w * total >> shift);
+}
+
+// the workgroup whose share holds block b: the largest w with w * total < (b + 1) << shift
+__device__ __forceinline__ unsigned share_of(unsigned b, unsigned total, int shift) {
+  if (total <= (1u << shift)) return b;
+  if (total < (1u << 20)) return (((b + 1u) << shift) - 1u) / total;
+  return (unsigned)(((((uint64_t)b + 1u) << shift) - 1u) / total);
 }
 
 __device__ __forceinline__ int64_t lane_i64(int64_t v, int src) {
@@ -192,8 +208,8 @@ __global__ __launch_bounds__(64 * kDecWaves, NG <= 4 ? (!F32 ? 4 : D == 64 ? 3 :
   const int64_t off_last = offsets[NH];
   const int64_t off_first = lane_i64(probe, 0);
   const DecShare sh = dec_share<T::kShift>(g, off_first, off_last);
-  unsigned f = blockIdx.x * sh.per;
-  const unsigned f_end = min(f + sh.per, sh.total);
+  unsigned f = share_begin(blockIdx.x, sh.total, g.wgs_shift);
+  const unsigned f_end = share_begin(blockIdx.x + 1, sh.total, g.wgs_shift);
   if (f >= f_end) return;
   int hi = 0;
   for (int n = NH;;) {
@@ -208,9 +224,9 @@ __global__ __launch_bounds__(64 * kDecWaves, NG <= 4 ? (!F32 ? 4 : D == 64 ? 3 :
   }
   hi = __builtin_amdgcn_readfirstlane(hi);
   // More rows than the last-level cache holds are read with non-temporal loads, which the memory
-  // serves at a higher rate (a plain read of 2 GiB: 6.2 against 7.0 TB/s): 2.8 M rows of 512 heads
-  // (1.43 GB) 257 -> 233 us.  Fewer may still be in the cache from the step before, and lose: 52 428
-  // rows (27 MB) 13.3 -> 14.1 us.  Groups in several passes read the rows again.
+  // serves at a higher rate (a plain read of 2 GiB: 6.2 against 7.0 TB/s): 1.43 GB 257 -> 234 us with 2048
+  // workgroups.  Fewer may still be in the cache from the step before, and lose: 27 MB 13.3 -> 14.1 us.
+  // Groups of more than eight take two passes and read the rows again.
   auto share = [&](auto stream_tag) __attribute__((always_inline)) {
   constexpr bool kStream = decltype(stream_tag)::value;
   for (; f < f_end && hi < NH; ++hi) {
@@ -391,8 +407,9 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecGeom g, const int
     return;
   }
   const unsigned b0 = (unsigned)((o0 >> SHIFT) - sh.first + hi), b1 = (unsigned)((o1 >> SHIFT) - sh.first + hi);
-  const unsigned last = (unsigned)g.n_wgs - 1u;          // (no limit but where offsets fall)
-  const int w0 = (int)min(b0 / sh.per, last), n_part = (int)min(b1 / sh.per, last) - w0 + 1;
+  const unsigned last = (1u << g.wgs_shift) - 1u;        // (no limit but where offsets fall)
+  const int w0 = (int)min(share_of(b0, sh.total, g.wgs_shift), last);
+  const int n_part = (int)min(share_of(b1, sh.total, g.wgs_shift), last) - w0 + 1;
   const float* hp = part + (((int64_t)w0 + hi) * G + gq) * (D + 2);
   const int64_t bstride = (int64_t)G * (D + 2);
   float m_run = -INFINITY, a = 0.f, l = 0.f;
@@ -447,7 +464,7 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecGeom g, const int
 // One slot per workgroup and head.  (Never less than what one slot per 128 rows of the longest
 // possible head takes, the size this query has always answered.)
 int64_t decode_workspace_bytes(const HostCfg& hc) {
-  const int64_t slots = (int64_t)hc.n_hi + dec_wgs(hc.g.group);
+  const int64_t slots = (int64_t)hc.n_hi + (1 << dec_wgs_shift(hc));
   const int64_t by_rows = (int64_t)hc.n_hi * ((hc.max_len + 127) / 128);
   return (slots > by_rows ? slots : by_rows) * hc.g.group * (hc.g.head_dim + 2) * 4;
 }
@@ -457,15 +474,16 @@ static int launch_decode_t(const HostCfg& hc, const void* q, const void* kp, con
                            const int64_t* offsets, float* out, char* ws, hipStream_t st) {
   constexpr int S = DecTile<F32, D>::kShift;
   const Geom& g = hc.g;
-  DecGeom dg{g.n_layers, g.n_q_heads, g.n_kv_heads, g.group, hc.seq.n_seqs, hc.n_hi, dec_wgs(NG),
+  DecGeom dg{g.n_layers, g.n_q_heads, g.n_kv_heads, g.group, hc.seq.n_seqs, hc.n_hi, dec_wgs_shift(hc),
              g.scale_log2e};
   float* part = reinterpret_cast<float*>(ws);
-  hipLaunchKernelGGL((decode_partial_kernel<F32, D, NG>), dim3(dg.n_wgs, (g.group + NG - 1) / NG),
+  hipLaunchKernelGGL((decode_partial_kernel<F32, D, NG>), dim3(1 << dg.wgs_shift, (g.group + NG - 1) / NG),
                      dim3(64 * kDecWaves), 0, st, dg, (const char*)q, (const char*)kp, (const char*)vp, offsets, part);
-  // Few heads, so many partial results of each: 32 groups share them and a workgroup takes 32
-  // columns (one workgroup for all 128 columns took 7.4 us for 8 heads with 104 partial results
-  // each, this takes 4.9); many heads: a handful of partial results each, little to share.
-  if (hc.n_hi <= 64)
+  // Few heads, so many partial results of each: 32 groups share them and a workgroup takes 32 columns
+  // (8 heads, 52 428 rows: 13.2 us a call against 17.5 with one workgroup for all columns).  Otherwise a
+  // handful of partial results each, little to share, and the groups' workgroups would queue (64 heads
+  // of 60 rows, G 4: 7.7 us against 11.0).
+  if (hc.n_hi <= 8 || (hc.n_hi <= 32 && hc.n_hi * g.group < 128))
     hipLaunchKernelGGL((decode_combine_kernel<D, S, 1024, 32, 4>), dim3(g.group, hc.n_hi, D / 32), dim3(1024), 0, st, dg,
                        offsets, (const float*)part, out);
   else
