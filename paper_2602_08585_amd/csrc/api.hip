@@ -130,12 +130,14 @@ int validate_config(const lukv_config* cfg, HostCfg* out) {
       return n * g.n_kv_heads * g.n_layers;
     };
     const int most = g.rows > 128 ? (g.f32 ? 448 : 512) : g.head_dim == 64 && !g.f32 ? 704 : g.head_dim == 128 && g.f32 ? 256 : 448;
-    while (g.accum_keys > 128 && g.accum_keys > g.chunk_keys / 4) {
-      const int64_t now = n_pieces(g.accum_keys), cut = n_pieces(g.accum_keys / 2);
-      if (now > 256 || cut > most || 2 * cut < 3 * now) break;
-      if (cut > 256 && 4 * (max_len - g.window) < 3 * g.accum_keys) break;
-      g.accum_keys /= 2;
-    }
+    // (a chunk of window positions alone has no piece with a key, but its workgroups are launched too)
+    auto fits = [&](int keys) {
+      const int64_t now = n_pieces(2 * keys), cut = n_pieces(keys), launched = n_wgs(g.chunk_keys) * (g.chunk_keys / keys);
+      return keys >= 128 && now <= 256 && launched <= most && 2 * cut >= 3 * now &&
+             (launched <= 256 || 4 * (max_len - g.window) >= 6 * keys);
+    };
+    if (fits(g.chunk_keys / 4)) g.accum_keys = g.chunk_keys / 4;
+    else if (fits(g.chunk_keys / 2)) g.accum_keys = g.chunk_keys / 2;
     g.accum_parts = g.chunk_keys / g.accum_keys;
     // The statistics kernel cannot (a granule's sum runs over its keys in order), so one workgroup
     // takes one block of 32 rows per wave group (not fewer groups: they fix the order of the keys), and
