@@ -37,7 +37,8 @@ constexpr int kDecWaves = 4;       // waves of a workgroup of decode_partial (th
 constexpr int64_t kDecStreamBytes = 256ll << 20;   // bytes of K and V from which they are streamed
 
 struct DecGeom {
-  int32_t n_layers, n_q_heads, n_kv_heads, group, n_seqs, n_heads_total, wgs_shift;   // (1 << wgs_shift workgroups)
+  int32_t n_layers, n_q_heads, n_kv_heads, group, n_seqs, n_heads_total;
+  int32_t wgs_shift, singles;   // 1 << wgs_shift shares, or a share per block up to `singles` blocks
   float scale_log2e;
 };
 
@@ -46,7 +47,13 @@ struct DecGeom {
 // of 8 heads 20.5 us with 2048, 17.2 with 512 (bf16, d 128, G 4), in float32 35.4 and 27.7 (one workgroup
 // per 128 rows: 23.2 and 30.9).  More heads than that are short ones, most often, and a workgroup meets
 // several, one after the other: 4096 heads of 90 rows 42.9 us with 512, 37.0 with 2048.
+// Up to 768 blocks are taken by as many workgroups where those are resident too (582 blocks of 16 heads
+// 11.6 us, in 512 shares 12.5).
 static int dec_wgs_shift(const HostCfg& hc) { return hc.n_hi <= 512 ? 9 : hc.g.group <= 4 ? 11 : 10; }
+static int dec_singles(const HostCfg& hc, int shift) {
+  const bool four = hc.g.head_dim == 64 || (!hc.g.f32 && hc.g.group <= 4);     // four workgroups a CU
+  return four && shift == 9 ? 768 : 1 << shift;
+}
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -99,7 +106,7 @@ struct DecTile {
 };
 
 // Block numbers of all heads, from `first`, the first head's, on.  Workgroup w takes the blocks from
-// w * total >> shift on (all shares equal or one apart), or block w if there are no more than workgroups.
+// w * total >> shift on (all shares equal or one apart), or block w up to `singles` blocks.
 struct DecShare { int64_t first; unsigned total; };
 
 template <int SHIFT>
@@ -110,15 +117,16 @@ __device__ __forceinline__ DecShare dec_share(const DecGeom& g, int64_t off_firs
   return s;
 }
 
-__device__ __forceinline__ unsigned share_begin(unsigned w, unsigned total, int shift) {
-  return total <= (1u << shift) ? min(w, total) : (unsigned)((uint64_t)w * total >> shift);
+__device__ __forceinline__ unsigned share_begin(const DecGeom& g, unsigned w, unsigned total) {
+  if (total <= (unsigned)g.singles) return min(w, total);
+  return w >> g.wgs_shift ? total : (unsigned)((uint64_t)w * total >> g.wgs_shift);
 }
 
-// the workgroup whose share holds block b: the largest w with w * total < (b + 1) << shift
-__device__ __forceinline__ unsigned share_of(unsigned b, unsigned total, int shift) {
-  if (total <= (1u << shift)) return b;
-  if (total < (1u << 20)) return (((b + 1u) << shift) - 1u) / total;
-  return (unsigned)(((((uint64_t)b + 1u) << shift) - 1u) / total);
+// the workgroup whose share holds block b: the largest w with w * total < (b + 1) << wgs_shift
+__device__ __forceinline__ unsigned share_of(const DecGeom& g, unsigned b, unsigned total) {
+  if (total <= (unsigned)g.singles) return b;
+  if (total < (1u << 20)) return (((b + 1u) << g.wgs_shift) - 1u) / total;
+  return (unsigned)(((((uint64_t)b + 1u) << g.wgs_shift) - 1u) / total);
 }
 
 __device__ __forceinline__ int64_t lane_i64(int64_t v, int src) {
@@ -208,8 +216,8 @@ __global__ __launch_bounds__(64 * kDecWaves, NG <= 4 ? (!F32 ? 4 : D == 64 ? 3 :
   const int64_t off_last = offsets[NH];
   const int64_t off_first = lane_i64(probe, 0);
   const DecShare sh = dec_share<T::kShift>(g, off_first, off_last);
-  unsigned f = share_begin(blockIdx.x, sh.total, g.wgs_shift);
-  const unsigned f_end = share_begin(blockIdx.x + 1, sh.total, g.wgs_shift);
+  unsigned f = share_begin(g, blockIdx.x, sh.total);
+  const unsigned f_end = share_begin(g, blockIdx.x + 1, sh.total);
   if (f >= f_end) return;
   int hi = 0;
   for (int n = NH;;) {
@@ -407,9 +415,9 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecGeom g, const int
     return;
   }
   const unsigned b0 = (unsigned)((o0 >> SHIFT) - sh.first + hi), b1 = (unsigned)((o1 >> SHIFT) - sh.first + hi);
-  const unsigned last = (1u << g.wgs_shift) - 1u;        // (no limit but where offsets fall)
-  const int w0 = (int)min(share_of(b0, sh.total, g.wgs_shift), last);
-  const int n_part = (int)min(share_of(b1, sh.total, g.wgs_shift), last) - w0 + 1;
+  const unsigned last = (unsigned)g.singles - 1u;        // (no limit but where offsets fall)
+  const int w0 = (int)min(share_of(g, b0, sh.total), last);
+  const int n_part = (int)min(share_of(g, b1, sh.total), last) - w0 + 1;
   const float* hp = part + (((int64_t)w0 + hi) * G + gq) * (D + 2);
   const int64_t bstride = (int64_t)G * (D + 2);
   float m_run = -INFINITY, a = 0.f, l = 0.f;
@@ -464,7 +472,7 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecGeom g, const int
 // One slot per workgroup and head.  (Never less than what one slot per 128 rows of the longest
 // possible head takes, the size this query has always answered.)
 int64_t decode_workspace_bytes(const HostCfg& hc) {
-  const int64_t slots = (int64_t)hc.n_hi + (1 << dec_wgs_shift(hc));
+  const int64_t slots = (int64_t)hc.n_hi + dec_singles(hc, dec_wgs_shift(hc));
   const int64_t by_rows = (int64_t)hc.n_hi * ((hc.max_len + 127) / 128);
   return (slots > by_rows ? slots : by_rows) * hc.g.group * (hc.g.head_dim + 2) * 4;
 }
@@ -475,15 +483,16 @@ static int launch_decode_t(const HostCfg& hc, const void* q, const void* kp, con
   constexpr int S = DecTile<F32, D>::kShift;
   const Geom& g = hc.g;
   DecGeom dg{g.n_layers, g.n_q_heads, g.n_kv_heads, g.group, hc.seq.n_seqs, hc.n_hi, dec_wgs_shift(hc),
+             dec_singles(hc, dec_wgs_shift(hc)),
              g.scale_log2e};
   float* part = reinterpret_cast<float*>(ws);
-  hipLaunchKernelGGL((decode_partial_kernel<F32, D, NG>), dim3(1 << dg.wgs_shift, (g.group + NG - 1) / NG),
+  hipLaunchKernelGGL((decode_partial_kernel<F32, D, NG>), dim3(dg.singles, (g.group + NG - 1) / NG),
                      dim3(64 * kDecWaves), 0, st, dg, (const char*)q, (const char*)kp, (const char*)vp, offsets, part);
   // Few heads, so many partial results of each: 32 groups share them and a workgroup takes 32 columns
   // (8 heads, 52 428 rows: 13.2 us a call against 17.5 with one workgroup for all columns).  Otherwise a
   // handful of partial results each, little to share, and the groups' workgroups would queue (64 heads
   // of 60 rows, G 4: 7.7 us against 11.0).
-  if (hc.n_hi <= 8 || (hc.n_hi <= 32 && hc.n_hi * g.group < 128))
+  if (hc.n_hi <= 8 || (hc.n_hi <= 32 && hc.n_hi * g.group <= 128))
     hipLaunchKernelGGL((decode_combine_kernel<D, S, 1024, 32, 4>), dim3(g.group, hc.n_hi, D / 32), dim3(1024), 0, st, dg,
                        offsets, (const float*)part, out);
   else
