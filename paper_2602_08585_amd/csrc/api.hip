@@ -121,8 +121,8 @@ int validate_config(const lukv_config* cfg, HostCfg* out) {
     // costs more than shorter pieces give (20000 tokens of 4 heads in float32: 57 us uncut, 63 with 316
     // pieces); beyond 128 rows a piece is work enough that the allocation's workgroups don't matter.
     // Above 256 pieces also only where most of a chunk has keys (256 heads of 310 tokens: 79 -> 84).
-    // One layer of 4001 tokens 43.1 us uncut, 38.7 in pieces of 128 keys; 8 heads of 131072, 16 rows:
-    // 60.9 -> 52.7; 24000 tokens and more of 8 heads: uncut.
+    // One layer of 4001 tokens 43.1 us uncut, 38.7 in pieces of 128 keys; one head of 131072, 8 rows:
+    // 60.9 -> 51.0; 24000 tokens and more of 8 heads: uncut.
     g.accum_keys = g.chunk_keys;
     auto n_pieces = [&](int keys) {
       int64_t n = 0;
